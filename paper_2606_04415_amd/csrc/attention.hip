@@ -537,7 +537,9 @@ void decode_gqa_kernel(AttnParams p) {
 //                    r0 + w*RB*16 .. +RB*16 of the tile.
 // LDS rows: grouped-query K/V rows are unpadded and XOR-swizzled by 16-byte
 // chunk so the MFMA operand reads are bank-conflict free; latent rows
-// (576 wide) are padded by one chunk instead.
+// (576 wide) are padded by two chunks instead: at 1184 bytes a row both the
+// key operand reads and the transposing value reads run at the full LDS rate
+// (256 bytes a clock; one chunk of padding, 1168 bytes, halves both).
 // ---------------------------------------------------------------------------
 enum RowMode { kPrefillGrouped = 0, kPrefillPerHead = 1, kDecodeLatent = 2, kPrefillFlat = 3 };
 
@@ -585,7 +587,7 @@ struct RowParCfg {
   static constexpr int DC = DQK / 32;
   static constexpr int CPR = DQK / 8;                      // 16-byte chunks of a K row
   static constexpr int CPRV = VALIAS ? 0 : DV / 8;         // of a separate V row
-  static constexpr int ROWB = VALIAS ? CPR + 1 : CPR;      // LDS K row stride, chunks
+  static constexpr int ROWB = VALIAS ? CPR + 2 : CPR;      // LDS K row stride, chunks
   static constexpr int K_SLOTS = BN * ROWB;
   static constexpr int SLOTS = K_SLOTS + BN * CPRV;
   static constexpr int TI_RAW = (SLOTS + 63) / 64;         // 1 KB loads per tile
@@ -1009,14 +1011,25 @@ __device__ __forceinline__ void rowpar_body(const AttnParams& p, int item, int c
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb) s[rb][2 * ch + b] = mfma_16x16x32(kop[b][c], qop[rb][c], s[rb][2 * ch + b]);
       } else {
+        // The compiler places each operand read right before its product
+        // and waits for it there, a full LDS latency per product: reads run
+        // KD products ahead instead, held in place by the scheduling
+        // barriers (4096-token latent prompt, with the row padding above:
+        // 2890 -> 2401 us; 256 latent decodes: 869 -> 752 us).
+        constexpr int KD = 4, NK = 2 * C::DC;
+        u32x4 kb[KD];
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+        for (int i = 0; i < KD; ++i) kb[i] = kread(stage, ch, i / C::DC, i % C::DC);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int c = 0; c < C::DC; ++c) {
-            const u32x4 kop = kread(stage, ch, b, c);
+        for (int i = 0; i < NK; ++i) {
+          const int b = i / C::DC, c = i % C::DC;
 #pragma unroll
-            for (int rb = 0; rb < RB; ++rb) s[rb][2 * ch + b] = mfma_16x16x32(kop, qop[rb][c], s[rb][2 * ch + b]);
-          }
+          for (int rb = 0; rb < RB; ++rb)
+            s[rb][2 * ch + b] = mfma_16x16x32(kb[i % KD], qop[rb][c], s[rb][2 * ch + b]);
+          if (i + KD < NK) kb[i % KD] = kread(stage, ch, (i + KD) / C::DC, (i + KD) % C::DC);
+          __builtin_amdgcn_sched_barrier(0);
+        }
       }
       // Keep each chunk's operand reads next to its products: hoisting every
       // read of the tile to the top would cost a register per value.
@@ -1091,13 +1104,33 @@ __device__ __forceinline__ void rowpar_body(const AttnParams& p, int item, int c
       }
       // Transposing LDS reads give each lane its 8 keys of value column
       // 16cv + n (keys 4gq + e and 16 + 4gq + e of the chunk).
+      if constexpr (VALIAS) {
+        constexpr int VD = 4;   // reads run VD products ahead (as for the keys)
+        u32x4 vb[VD];
+        auto vop_read = [&](int cv) {
+          const u32x2 lo = vread(stage, ch, 0, cv);
+          const u32x2 hi = vread(stage, ch, 1, cv);
+          return u32x4{lo[0], lo[1], hi[0], hi[1]};
+        };
 #pragma unroll
-      for (int cv = 0; cv < C::NACC; ++cv) {
-        const u32x2 lo = vread(stage, ch, 0, cv);
-        const u32x2 hi = vread(stage, ch, 1, cv);
-        const u32x4 vop = {lo[0], lo[1], hi[0], hi[1]};
+        for (int cv = 0; cv < VD; ++cv) vb[cv] = vop_read(cv);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) o[rb][cv] = mfma_16x16x32(pop[rb], vop, o[rb][cv]);
+        for (int cv = 0; cv < C::NACC; ++cv) {
+#pragma unroll
+          for (int rb = 0; rb < RB; ++rb) o[rb][cv] = mfma_16x16x32(pop[rb], vb[cv % VD], o[rb][cv]);
+          if (cv + VD < C::NACC) vb[cv % VD] = vop_read(cv + VD);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      } else {
+#pragma unroll
+        for (int cv = 0; cv < C::NACC; ++cv) {
+          const u32x2 lo = vread(stage, ch, 0, cv);
+          const u32x2 hi = vread(stage, ch, 1, cv);
+          const u32x4 vop = {lo[0], lo[1], hi[0], hi[1]};
+#pragma unroll
+          for (int rb = 0; rb < RB; ++rb) o[rb][cv] = mfma_16x16x32(pop[rb], vop, o[rb][cv]);
+        }
       }
       __builtin_amdgcn_sched_barrier(0);
     }
