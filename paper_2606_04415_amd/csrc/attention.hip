@@ -1516,11 +1516,10 @@ static hipError_t launch_decode_kernel(const AttnParams& p, int dqk, hipStream_t
   switch (dqk) {
     case 128: return p16 ? launch_decode_gqa<128, 16>(p, stream) : launch_decode_gqa<128, 64>(p, stream);
     case 64: return p16 ? launch_decode_gqa<64, 16>(p, stream) : launch_decode_gqa<64, 64>(p, stream);
-    case 576:   // one work-group per (piece, group of 128 or 64 heads), a wave per 16 heads;
-                // 64-head groups take two LDS stages so that two work-groups share a CU
+    case 576:   // one work-group per (piece, group of 128 or 64 heads): 128 heads on four waves of 32;
+                // 64 on four of 16, with two LDS stages so that two work-groups share a CU
       if (p.rows_per_wg == 128)
-        return p16 ? launch_rowpar<576, 512, 8, 1, 32, true, kDecodeLatent, 16, 3>(p, pieces, stream)
-                   : launch_rowpar<576, 512, 8, 1, 32, true, kDecodeLatent, 64, 3>(p, pieces, stream);
+        return launch_latent128(p, true, pieces, stream);
       return p16 ? launch_rowpar<576, 512, 4, 1, 32, true, kDecodeLatent, 16, 2>(p, pieces, stream)
                  : launch_rowpar<576, 512, 4, 1, 32, true, kDecodeLatent, 64, 2>(p, pieces, stream);
     default: return hipErrorInvalidValue;
@@ -1633,14 +1632,14 @@ static hipError_t launch_prefill_p(const AttnParams& p, int dqk, int bm, dim3 gr
     AttnParams q = p;
     q.xcd_remap = 1;
     const dim3 g1(p.n_items * p.grid_y, 1);
-    if (dqk == 576 && bm == 128) return launch_rowpar<576, 512, 8, 1, 32, true, kPrefillPerHead, P, 3>(q, g1, stream);
+    if (dqk == 576 && bm == 128) return launch_latent128(q, false, g1, stream);
     if (dqk == 576 && bm == 64) return launch_rowpar<576, 512, 4, 1, 32, true, kPrefillPerHead, P, 2>(q, g1, stream);
     if constexpr (P == 64) {
       if (dqk == 192 && bm == 128) return launch_perhead_t<192, 128, 4, 2, 32, 64, 3, 2>(q, g1, stream);
     }
     return hipErrorInvalidValue;
   }
-  if (dqk == 576 && bm == 128) return launch_rowpar<576, 512, 8, 1, 32, true, kPrefillPerHead, P, 3>(p, grid, stream);
+  if (dqk == 576 && bm == 128) return launch_latent128(p, false, grid, stream);
   if (dqk == 576 && bm == 64) return launch_rowpar<576, 512, 4, 1, 32, true, kPrefillPerHead, P, 2>(p, grid, stream);
   // Heads split out (keys 192, values 128): one work-group per (128-token
   // tile, query head), four waves of 32 rows (two 16-row blocks each, so
