@@ -7,7 +7,8 @@
 //                     K and V from HBM into registers (K through a wave-private
 //                     LDS buffer that turns whole-line loads into MFMA rows).
 // rowpar_kernel       prefill phase (all layouts) and decode of the 576/512
-//                     latent layout: each wave owns 16 or 32 query rows; the
+//                     latent layout in groups of 64 rows (groups of 128 have
+//                     a kernel of their own, latent.hip): each wave owns 16 or 32 query rows; the
 //                     work-group streams key tiles, gathered through the block
 //                     table, into a ring of LDS stages shared by all waves.
 //                     flat_prefill_kernel (grouped-query rows of one KV head)
@@ -39,12 +40,18 @@ __device__ __forceinline__ PagedCache as_cache(const CacheRef& c) { return Paged
 // running maximum M: results are bit-identical run to run. The result is
 //   out = sum_j 2^{m_j - M} O_j / sum_j 2^{m_j - M} l_j,
 //   lse = (M + log2 sum_j 2^{m_j - M} l_j) * ln 2     (m_j in log2 units).
-template <int DV>
-__global__ __launch_bounds__(256) void merge_kernel(AttnParams p) {
-  constexpr int KB = 8;   // pieces folded per step
-  const int32_t* it = p.items + 8 * p.merge[blockIdx.x];   // the sequence's first piece
+//
+// Bound by HBM reads of the partials. Loads past the last piece repeat it, so
+// a sequence takes the smallest step that holds its pieces: with steps of 8
+// throughout, a sequence of two pieces issued four times the loads it needs,
+// and (with at most 8 slices of the rows per sequence) 256 latent decodes in
+// 128-head groups took 51 us; now 37 us (24 in 64-head
+// groups 14.2, now 8.7). One step covers every sequence of up to 8 pieces, so
+// the sums' order does not depend on the step.
+template <int DV, int KB>
+__device__ __forceinline__ void merge_rows(const AttnParams& p, const int32_t* it, int col, int W) {
   const int slot0 = it[5], nspl = it[2];   // workspace slots slot0 .. slot0 + nspl - 1
-  const int col = blockIdx.y, W = gridDim.y, rows = p.rows_per_wg;
+  const int rows = p.rows_per_wg;
   const int64_t out_row0 = int64_t(it[6]) * p.Hq + int64_t(col) * rows;
   for (int idx = blockIdx.z * blockDim.x + threadIdx.x; idx < rows * (DV / 4); idx += blockDim.x * gridDim.z) {
     const int i = idx / (DV / 4);
@@ -83,6 +90,15 @@ __global__ __launch_bounds__(256) void merge_kernel(AttnParams p) {
     *reinterpret_cast<u32x2*>(p.out + (out_row0 + i) * DV + d) = pk;
     if (d == 0 && p.lse) p.lse[out_row0 + i] = (M + log2f(den)) * kLn2;
   }
+}
+
+template <int DV>
+__global__ __launch_bounds__(256) void merge_kernel(AttnParams p) {
+  const int32_t* it = p.items + 8 * p.merge[blockIdx.x];   // the sequence's first piece
+  const int col = blockIdx.y, W = gridDim.y;
+  if (it[2] <= 2) merge_rows<DV, 2>(p, it, col, W);
+  else if (it[2] <= 4) merge_rows<DV, 4>(p, it, col, W);
+  else merge_rows<DV, 8>(p, it, col, W);
 }
 
 // Block-table entries of one work-group's key range are staged in LDS in
@@ -1014,8 +1030,8 @@ __device__ __forceinline__ void rowpar_body(const AttnParams& p, int item, int c
         // The compiler places each operand read right before its product
         // and waits for it there, a full LDS latency per product: reads run
         // KD products ahead instead, held in place by the scheduling
-        // barriers (4096-token latent prompt, with the row padding above:
-        // 2890 -> 2401 us; 256 latent decodes: 869 -> 752 us).
+        // barriers (64-head mixed latent step, with the row padding above:
+        // 267 -> 215 us, its decodes now 44 us).
         constexpr int KD = 4, NK = 2 * C::DC;
         u32x4 kb[KD];
 #pragma unroll
@@ -1527,13 +1543,14 @@ static hipError_t launch_decode_kernel(const AttnParams& p, int dqk, hipStream_t
 }
 
 // Merge: one work-group per (split sequence, column, slice of the output
-// rows), each thread at most a few (row, 4 columns) outputs so all their
-// loads are in flight together.
+// rows), a thread per (row, 4 columns) output up to 64 slices, which covers
+// the largest column (128 latent rows), so that all loads are in flight
+// together.
 static hipError_t launch_merge(const AttnParams& p, int dqk, hipStream_t stream) {
   if (p.n_merge == 0) return hipSuccess;
   const int dv = dqk == 576 ? 512 : dqk;
   const int units = p.rows_per_wg * (dv / 4);
-  const dim3 mgrid(p.n_merge, p.grid_y, std::min(8, (units + 255) / 256));
+  const dim3 mgrid(p.n_merge, p.grid_y, std::min(64, (units + 255) / 256));
   switch (dqk) {
     case 128: hipLaunchKernelGGL(merge_kernel<128>, mgrid, dim3(256), 0, stream, p); break;
     case 64: hipLaunchKernelGGL(merge_kernel<64>, mgrid, dim3(256), 0, stream, p); break;
