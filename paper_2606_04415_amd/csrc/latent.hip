@@ -89,8 +89,14 @@ __device__ __forceinline__ void mfma_agpr(f32x16& d, const u32x4& a, const u32x4
   asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(a), "v"(b));
 }
 __device__ __forceinline__ void product_wait() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
-// The scores may be read from here on (keeps their readers below this point).
+// The scores (accumulators) may be read from here on. The wait alone does not
+// keep plain reads of them below it: their values have to pass through here.
 __device__ __forceinline__ void scores_ready(f32x16& s) { asm volatile("" : "+v"(s)); }
+template <int N>
+__device__ __forceinline__ void accumulators_ready(f32x16 (&o)[N]) {
+#pragma unroll
+  for (int a = 0; a < N; ++a) asm volatile("" : "+a"(o[a]));
+}
 
 __device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
 
@@ -288,6 +294,7 @@ void latent_kernel(AttnParams p) {
   };
   auto do_rescale = [&]() {
     product_wait();
+    accumulators_ready(o);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const float ar = shfl_f(alpha, 8 * (r >> 2) + 4 * h + (r & 3));
@@ -412,6 +419,7 @@ void latent_kernel(AttnParams p) {
 
   // Epilogue: register 4i + r of a lane holds row 8i + 4h + r of the wave.
   product_wait();
+  accumulators_ready(o);
   if (!wave_on) return;
   const float ltot = half_sum(l);
   const int vlane = (n & 15) + 64 * (n >> 4);   // column of the lane in a value block
