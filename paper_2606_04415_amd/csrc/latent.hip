@@ -186,10 +186,11 @@ void latent_kernel(AttnParams p) {
   // Loads of a tile: the wave's 8 rows lie in one page, so one resource on
   // the page serves all nine. Lane i of a row load takes 16-byte chunk i of
   // the row (i ^ 1 in rows 16 to 31); of the tail load, chunk
-  // 64 + ((i & 7) ^ swizzle) of row i >> 3. The record count ends at the
-  // tile's last key: rows past it read as zeros and touch no memory. Tiles
-  // past the window get empty resources: their loads are issued all the
-  // same, so that wait counts are fixed.
+  // 64 + ((i & 7) ^ swizzle) of row i >> 3. The record count ends with the
+  // row of the tile's last key (a whole row past its start: the slot stride
+  // may be less than a row), so what is read past it reads as zeros and
+  // touches no memory. Tiles past the window get empty resources: their loads
+  // are issued all the same, so that wait counts are fixed.
   const uint32_t ld_row = 16u * uint32_t(lane ^ (w >> 1));
   const uint32_t ld_tail =
       uint32_t(lane >> 3) * kss + 1024u + 16u * uint32_t((lane & 7) ^ (((8 * w + (lane >> 3)) >> 1) & 7));
@@ -197,9 +198,10 @@ void latent_kernel(AttnParams p) {
   auto source = [&](int kb, int end, int page) {
     const int g0 = kb + 8 * w;
     const uint64_t a = reinterpret_cast<uint64_t>(kbase + (uint64_t(uint32_t(page)) * ksp + uint32_t(g0 % P) * kss));
+    const int rows = min(8, end - g0);
     i32x4 r = {__builtin_amdgcn_readfirstlane(int32_t(uint32_t(a))),
                __builtin_amdgcn_readfirstlane(int32_t(uint32_t(a >> 32) & 0xFFFFu)),
-               __builtin_amdgcn_readfirstlane(int32_t(uint32_t(max(0, min(8, end - g0))) * kss)), kBufferFlags};
+               __builtin_amdgcn_readfirstlane(rows > 0 ? int32_t(uint32_t(rows - 1) * kss + 2 * kQK) : 0), kBufferFlags};
     // A vector instruction's scalar result needs 5 wait states before a
     // memory instruction reads it; the loads below are opaque to the compiler.
     asm volatile("s_nop 4" : "+s"(r));
