@@ -49,12 +49,11 @@ constexpr int kTailOff = kBN * kRow;
 constexpr int kStage = kTailOff + kBN * 128;
 constexpr int kLoads = 9;                // loads of a wave per tile
 // A row's maximum moves only when a tile raises it by more than this many
-// log2 units. Probabilities then reach 2^24 and sums 2^41 over 128 K keys,
-// far inside the range that bf16 and fp32 share, and neither loses precision
-// to a common factor. Rescaling 256 accumulation registers costs 3000 clocks,
-// more than a tile, and the barrier makes all four waves wait for it: with a
-// threshold of 8 the 4096-token prompt took 3310 us, with this one 2012.
-constexpr float kRescale = 24.0f;
+// log2 units, as in the other row-parallel kernels. A fresher maximum is not
+// only a matter of range: a row's largest probability is exactly 1 while it
+// is the maximum, and rounded to bf16 otherwise (with 24 units here the error
+// of the log-sum-exp against 64 bits is 1.3 times as large).
+constexpr float kRescale = 8.0f;
 constexpr int kWin = 2048;               // block-table entries held in LDS
 constexpr int kLds = kStages * kStage + kWin * 4;
 static_assert(kLds <= 160 * 1024, "LDS of a compute unit");
@@ -99,6 +98,44 @@ __device__ __forceinline__ void accumulators_ready(f32x16 (&o)[N]) {
 }
 
 __device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
+
+// Scales register R of every accumulator if one of the two rows it holds (ROW
+// in the low half of the wave, ROW + 4 in the high half) is set in `rows`, by
+// the factors that lanes ROW and ROW + 4 hold in alpha. The branch is inside
+// the block because the compiler, given a branch per register, copies all
+// accumulators at each. The waits are those between a vector instruction that
+// writes a scalar (or alpha) and the one that reads it.
+template <int R>
+__device__ __forceinline__ void scale_register(f32x16 (&o)[kACC], uint32_t rows, float alpha) {
+  constexpr int ROW = 8 * (R >> 2) + (R & 3);
+  static_assert(kACC == 16, "operands below");
+  float f, t, v[kACC];
+  uint32_t s0, s1;
+#pragma unroll
+  for (int a = 0; a < kACC; ++a) v[a] = o[a][R];
+  asm volatile(
+      "s_and_b32 %[s0], %[rows], %[bits]\n\t"
+      "s_cbranch_scc0 .Lscaled_%=\n\t"
+      "v_readlane_b32 %[s0], %[alpha], %[row]\n\t"
+      "v_readlane_b32 %[s1], %[alpha], %[row] + 4\n\t"
+      "s_nop 1\n\t"
+      "v_mov_b32 %[f], %[s0]\n\t"
+      "v_mov_b32 %[t], %[s1]\n\t"
+      "v_cndmask_b32_e64 %[f], %[f], %[t], %[high]\n\t"
+      ".irp reg, %0, %1, %2, %3, %4, %5, %6, %7, %8, %9, %10, %11, %12, %13, %14, %15\n\t"
+      "v_accvgpr_read_b32 %[t], \\reg\n\t"
+      "v_mul_f32 %[t], %[t], %[f]\n\t"
+      "v_accvgpr_write_b32 \\reg, %[t]\n\t"
+      ".endr\n\t"
+      ".Lscaled_%=:"
+      : "+a"(v[0]), "+a"(v[1]), "+a"(v[2]), "+a"(v[3]), "+a"(v[4]), "+a"(v[5]), "+a"(v[6]), "+a"(v[7]), "+a"(v[8]),
+        "+a"(v[9]), "+a"(v[10]), "+a"(v[11]), "+a"(v[12]), "+a"(v[13]), "+a"(v[14]), "+a"(v[15]), [f] "=&v"(f),
+        [t] "=&v"(t), [s0] "=&s"(s0), [s1] "=&s"(s1)
+      : [rows] "s"(rows), [alpha] "v"(alpha), [high] "s"(0xFFFFFFFF00000000ull), [bits] "n"(0x11u << ROW), [row] "n"(ROW)
+      : "scc");
+#pragma unroll
+  for (int a = 0; a < kACC; ++a) o[a][R] = v[a];
+}
 
 // Max over the two halves of the wave, on the VALU.
 __device__ __forceinline__ float half_max(float v) { return swap32_combine_max(v); }
@@ -261,7 +298,7 @@ void latent_kernel(AttnParams p) {
   // (and alpha, its accumulators' factor, set) only when the tile raises it
   // by more than kRescale.
   float x[16];
-  bool rescale = false;
+  uint32_t moved_rows = 0;   // rows of the wave whose accumulators are due their factor
   auto mask = [&](f32x16& s, int kc0) {
 #pragma unroll
     for (int e = 0; e < 16; ++e) s[e] = kc0 + 8 * (e >> 2) + 4 * h + (e & 3) < row_limit ? s[e] : -INFINITY;
@@ -281,7 +318,7 @@ void latent_kernel(AttnParams p) {
     alpha = exp2_fast(m - m_new);   // 1 if unchanged
     m = m_new;
     l *= alpha;   // the sums of the tiles before; the accumulators follow in do_rescale
-    rescale = __builtin_amdgcn_ballot_w64(moved) != 0;
+    moved_rows = uint32_t(__builtin_amdgcn_ballot_w64(moved));   // (both halves hold the same rows)
   };
   auto exponent = [&](const f32x16& s, int e) { x[e] = fmaf(s[e], p.scale_log2, -m); };
 
@@ -294,21 +331,14 @@ void latent_kernel(AttnParams p) {
     pop[j >> 2][j & 3] = pk;
     l = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(short2v, pk), __builtin_bit_cast(short2v, 0x3F803F80u), l, false);
   };
+  // Only registers of a row that moved are scaled, 48 instructions each (an
+  // accumulation register passes through a vector register to be
+  // multiplied): all 16 cost 3000 clocks, more than a tile, and usually one
+  // or two of the 32 rows move.
   auto do_rescale = [&]() {
     product_wait();
     accumulators_ready(o);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const float ar = shfl_f(alpha, 8 * (r >> 2) + 4 * h + (r & 3));
-#pragma unroll
-      for (int a = 0; a < kACC; ++a) {
-        float t, v = o[a][r];
-        asm volatile("v_accvgpr_read_b32 %1, %0\n\tv_mul_f32 %1, %1, %2\n\tv_accvgpr_write_b32 %0, %1"
-                     : "+a"(v), "=&v"(t)
-                     : "v"(ar));
-        o[a][r] = v;
-      }
-    }
+    static_for<16>([&](auto rc) { scale_register<rc>(o, moved_rows, alpha); });
     product_wait();
   };
 
@@ -393,7 +423,7 @@ void latent_kernel(AttnParams p) {
           prob_hi(j);
         }
       }
-      if (rescale) do_rescale();
+      if (moved_rows) do_rescale();
       const int kc1 = wk0 + (t + 1) * kBN;
       if (kc1 + kBN > wave_full) {
         product_wait();

@@ -12,7 +12,7 @@ import pytest
 
 from paper_2606_04415_amd import build as B
 
-READ = re.compile(r"v_accvgpr_(?:read|mov)\w* \w+, a(\d+)$")
+READ = re.compile(r"v_accvgpr_(?:read|mov)\w* \w+, (?:a(\d+)|\\reg)$")   # \reg: the accumulators of a repeated line
 PRODUCT = re.compile(r"v_mfma\S+ a\[(\d+):(\d+)\]")
 BRANCH = re.compile(r"s_(c?branch)\w* (\.L\w+)")
 
@@ -47,7 +47,7 @@ def early_reads(lines):
             before[i + 1].append(i)
     results = {r for l in lines for m in [PRODUCT.match(l)] if m for r in range(int(m[1]), int(m[2]) + 1)}
     assert len(results) == 256, "the accumulators of 512 value columns"
-    reads = [i for i, l in enumerate(lines) for m in [READ.match(l)] if m and int(m[1]) in results]
+    reads = [i for i, l in enumerate(lines) for m in [READ.match(l)] if m and (m[1] is None or int(m[1]) in results)]
     assert reads
     early = []
     for i in reads:
