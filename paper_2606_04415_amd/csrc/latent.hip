@@ -54,6 +54,11 @@ constexpr int kLoads = 9;                // loads of a wave per tile
 // is the maximum, and rounded to bf16 otherwise (with 24 units here the error
 // of the log-sum-exp against 64 bits is 1.3 times as large).
 constexpr float kRescale = 8.0f;
+// Prefill tiles of few rows take 16 a wave instead of 32, so that twice as many
+// waves share the output's conversion and stores, if they are short enough for
+// that to count: 32 rows of 32 keys 9.6 -> 8.6 us, 64 rows of 64 keys 13.1 ->
+// 12.1, at 500 keys alike, at 4000 the further waves' LDS reads cost 0.5%.
+constexpr int kSpreadRows = 64, kSpreadKeys = 256;
 constexpr int kWin = 2048;               // block-table entries held in LDS
 constexpr int kLds = kStages * kStage + kWin * 4;
 static_assert(kLds <= 160 * 1024, "LDS of a compute unit");
@@ -98,6 +103,14 @@ __device__ __forceinline__ void accumulators_ready(f32x16 (&o)[N]) {
 }
 
 __device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
+
+// One element of an accumulator (read this way because the compiler moves whole
+// accumulators to vector registers for plain reads of their elements).
+__device__ __forceinline__ float acc_read(float a) {
+  float v;
+  asm("v_accvgpr_read_b32 %0, %1" : "=v"(v) : "a"(a));
+  return v;
+}
 
 // Scales register R of every accumulator if one of the two rows it holds (ROW
 // in the low half of the wave, ROW + 4 in the high half) is set in `rows`, by
@@ -179,6 +192,7 @@ void latent_kernel(AttnParams p) {
   const int it2 = scalar_word(p.items, it + 2), it3 = scalar_word(p.items, it + 3), it4 = scalar_word(p.items, it + 4);
   int key_begin, key_end, head_kv, wave_limit, wave_full;
   bool wave_on = true;
+  int wave_rows = 32;   // rows of the tile that a wave takes
   int row_limit;
   const uint16_t* q_row;
   if constexpr (DECODE) {
@@ -191,12 +205,14 @@ void latent_kernel(AttnParams p) {
     key_begin = 0;
     key_end = it4;
     head_kv = col / p.G;
-    const int wr0 = it2 + w * 32;
+    if (it3 - it2 <= kSpreadRows && it4 <= kSpreadKeys) wave_rows = 16;
+    const int wr0 = it2 + w * wave_rows;
+    const int wr1 = min(it3, wr0 + wave_rows);
     wave_on = wr0 < it3;
-    const int lr = wr0 + n < it3 ? wr0 + n : wr0;
+    const int lr = wr0 + n < wr1 ? wr0 + n : wr0;
     q_row = p.q + (int64_t(q0 + (wave_on ? lr : it2)) * p.Hq + col) * kQK;
     row_limit = L - nq + lr + 1;
-    wave_limit = wave_on ? L - nq + min(it3, wr0 + 32) : 0;
+    wave_limit = wave_on ? L - nq + wr1 : 0;
     wave_full = L - nq + wr0 + 1;
   }
 
@@ -227,7 +243,8 @@ void latent_kernel(AttnParams p) {
   // row of the tile's last key (a whole row past its start: the slot stride
   // may be less than a row), so what is read past it reads as zeros and
   // touches no memory. Tiles past the window get empty resources: their loads
-  // are issued all the same, so that wait counts are fixed.
+  // are issued all the same between the score products, where a branch per
+  // load would cost more.
   const uint32_t ld_row = 16u * uint32_t(lane ^ (w >> 1));
   const uint32_t ld_tail =
       uint32_t(lane >> 3) * kss + 1024u + 16u * uint32_t((lane & 7) ^ (((8 * w + (lane >> 3)) >> 1) & 7));
@@ -382,10 +399,19 @@ void latent_kernel(AttnParams p) {
 #pragma unroll
       for (int j = 0; j < kLoads; ++j) load_one(s, t & (kStages - 1), j);
     };
+    // Tile t + 1 of iteration t (or tile 0 here) has landed once at most the
+    // loads of the tiles after it are outstanding. Close to the end those may
+    // not have been issued: then for all.
 #pragma unroll
-    for (int t = 0; t < kStages - 1; ++t) load_tile(t);
-    wait_vmem<2 * kLoads>();
+    for (int t = 0; t < kStages - 1; ++t)
+      if (t < ntiles) load_tile(t);
+    if (ntiles > 2) wait_vmem<2 * kLoads>();
+    else wait_vmem_all();
     lds_barrier();
+    auto wait_next = [&](int t) {
+      if (t + 2 < ntiles) wait_vmem<kLoads>();
+      else wait_vmem_all();
+    };
     f32x16 s;
     if (mine > 0) {
       scores(stage_of(0), s, nothing);
@@ -400,7 +426,7 @@ void latent_kernel(AttnParams p) {
     }
     int t = 0;
     for (; t < mine; ++t) {
-      wait_vmem<kLoads>();
+      wait_next(t);
       lds_barrier();
       if (t + 1 < mine) {
         const int pgv = page_at(t + 3);
@@ -413,7 +439,7 @@ void latent_kernel(AttnParams p) {
           if constexpr (i % 4 == 3 && i < 32) prob_hi(i / 4);
         });
       } else {   // the wave's last tile: s stays, and its maxima move nothing when formed again
-        load_tile(t + 3);
+        if (t + 3 < ntiles) load_tile(t + 3);
         // (opaque, or the compiler forms both branches' exponentials ahead of the branch)
 #pragma unroll
         for (int e = 0; e < 16; ++e) asm volatile("" : "+v"(x[e]));
@@ -442,9 +468,9 @@ void latent_kernel(AttnParams p) {
       });
     }
     for (; t < ntiles; ++t) {   // past this wave's rows: loads and barriers only
-      wait_vmem<kLoads>();
+      wait_next(t);
       lds_barrier();
-      load_tile(t + 3);
+      if (t + 3 < ntiles) load_tile(t + 3);
     }
     wait_vmem_all();   // nothing may land in LDS after the work-group ends
   }
@@ -452,33 +478,76 @@ void latent_kernel(AttnParams p) {
   // Epilogue: register 4i + r of a lane holds row 8i + 4h + r of the wave.
   product_wait();
   accumulators_ready(o);
+  lds_barrier();   // the stages are free: output rows pass through them
   if (!wave_on) return;
   const float ltot = half_sum(l);
-  const int vlane = (n & 15) + 64 * (n >> 4);   // column of the lane in a value block
+  const int row0 = w * wave_rows;   // the wave's first row of the tile; the lane's row of m and l is row0 + n
+  if (DECODE && it2 > 1) {   // a split's partial
+    const int64_t srow0 = (int64_t(scalar_word(p.items, it + 7)) * int(gridDim.y) + col) * p.rows_per_wg;
+    const int vlane = (n & 15) + 64 * (n >> 4);   // column of the lane in a value block
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int rl = 8 * (r >> 2) + 4 * h + (r & 3);
-    const int rowi = w * 32 + rl;
-    const float mr = shfl_f(m, rl), lr = shfl_f(ltot, rl);
-    if (DECODE && it2 > 1) {   // a split's partial
-      const int64_t srow = (int64_t(scalar_word(p.items, it + 7)) * int(gridDim.y) + col) * p.rows_per_wg + rowi;
-      float* dst = p.ws_o + srow * kV + vlane;
+    for (int r = 0; r < 16; ++r) {
+      float* dst = p.ws_o + (srow0 + row0 + 8 * (r >> 2) + 4 * h + (r & 3)) * kV + vlane;
 #pragma unroll
-      for (int cv = 0; cv < kACC; ++cv) dst[vcol(cv)] = o[cv][r];
-      if (n == 0) {
-        p.ws_stats[srow * 2] = mr;
-        p.ws_stats[srow * 2 + 1] = lr;
-      }
-    } else if (DECODE || it2 + rowi < it3) {
-      const int64_t orow = DECODE ? int64_t(q0) * p.Hq + int64_t(col) * p.rows_per_wg + rowi
-                                  : int64_t(q0 + it2 + rowi) * p.Hq + col;
-      const float inv = 1.f / lr;
-      uint16_t* dst = p.out + orow * kV + vlane;
-#pragma unroll
-      for (int cv = 0; cv < kACC; ++cv) dst[vcol(cv)] = __builtin_bit_cast(uint16_t, (__bf16)(o[cv][r] * inv));
-      if (n == 0 && p.lse) p.lse[orow] = (mr + log2f(lr)) * kLn2;
+      for (int cv = 0; cv < kACC; ++cv) dst[vcol(cv)] = acc_read(o[cv][r]);
     }
+    if (h == 0) {
+      p.ws_stats[(srow0 + row0 + n) * 2] = m;
+      p.ws_stats[(srow0 + row0 + n) * 2 + 1] = ltot;
+    }
+    return;
   }
+  const int64_t out0 = DECODE ? int64_t(q0) * p.Hq + int64_t(col) * p.rows_per_wg : int64_t(q0 + it2) * p.Hq + col;
+  const int row_step = DECODE ? 1 : p.Hq;   // output rows between neighbouring rows of the tile
+  const int rows = DECODE ? 32 : min(wave_rows, it3 - it2 - row0);   // of the wave
+  if (h == 0 && n < rows && p.lse) p.lse[out0 + int64_t(row0 + n) * row_step] = (m + log2f(ltot)) * kLn2;
+  // Rows leave through LDS, eight at a time: a lane writes the columns it holds
+  // of one row in four neighbouring value blocks (8 bytes), and a transposing
+  // read gives it four neighbouring columns of that row, so that a store
+  // instruction covers two rows of 256 contiguous bytes. Two bytes a lane
+  // straight from the registers, four times as many stores, bound short calls:
+  // a decode over 20 keys 13.0 -> 11.5 us, a 128-token prompt 19.2 -> 18.3.
+  // (Four rows of 128 bytes in one instruction, neighbouring lanes in
+  // different rows, are slower than either: 15.7 and 22.5.)
+  constexpr int kOutBuf = 16 * 512;   // 16 reads of 64 lanes x 8 bytes, twice
+  static_assert(kNW * 2 * kOutBuf <= kStages * kStage, "output rows fit the stages");
+  uint8_t* buf = lds + w * 2 * kOutBuf;
+  const uint32_t rd = uint32_t(128 * (lane >> 4) + 8 * (4 * (lane & 3) + ((lane & 15) >> 2)));
+  const int col0 = 64 * (n >> 4) + 16 * (lane & 3) + 4 * ((lane & 15) >> 2);
+  const float inv_n = 1.f / ltot;
+  static_for<4>([&](auto ic) {
+    constexpr int i = ic;
+    if (8 * i >= rows) return;
+    uint8_t* half_buf = buf + (i & 1) * kOutBuf;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float inv = shfl_f(inv_n, 8 * i + 4 * h + r);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const int e = 4 * i + r;
+        const u32x2 d = {pack_bf16x2(acc_read(o[4 * c][e]) * inv, acc_read(o[4 * c + 1][e]) * inv),
+                         pack_bf16x2(acc_read(o[4 * c + 2][e]) * inv, acc_read(o[4 * c + 3][e]) * inv)};
+        *reinterpret_cast<u32x2*>(half_buf + (4 * r + c) * 512 + 8 * lane) = d;
+      }
+    }
+    wave_lds_sync();
+    u32x2 v[4][4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        v[r][c] = lds_read_tr16(reinterpret_cast<const uint16_t*>(half_buf + rd + (4 * r + c) * 512));
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = 8 * i + 4 * h + r;
+      uint16_t* dst = p.out + (out0 + int64_t(row0 + row) * row_step) * kV + col0;
+      if (row < rows) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) *reinterpret_cast<u32x2*>(dst + 128 * c) = v[r][c];
+      }
+    }
+  });
 }
 
 template <bool DECODE, int P>

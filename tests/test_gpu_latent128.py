@@ -22,6 +22,8 @@ CASES = {
     "decode-edges": ([1] * 12, [1, 7, 8, 9, 31, 32, 33, 63, 65, 96, 97, 129], 16),
     # rows around a wave's 32 and a tile's 128, with and without cached keys
     "prefill-edges": ([1, 31, 32, 33, 127, 128, 129, 2], [1, 31, 37, 33, 130, 128, 200, 95], 128),
+    # around the tiles that take 16 rows a wave: up to 64 rows and 256 keys
+    "prefill-spread": ([15, 16, 17, 47, 49, 64, 65, 64, 64], [15, 30, 17, 60, 49, 64, 65, 256, 257], 128),
     # 2, 3, 5 and 9 pieces of one sequence: every step of the merge
     "merge-steps": ([1, 1, 1, 1], [128, 192, 320, 1100], 64),
 }
