@@ -27,6 +27,7 @@
 
 #include "device_common.h"
 #include "kernels.h"
+#include "latent_tile.h"
 
 namespace flexattn {
 
@@ -553,13 +554,9 @@ void decode_gqa_kernel(AttnParams p) {
 //                    r0 + w*RB*16 .. +RB*16 of the tile.
 // LDS rows: grouped-query K/V rows are unpadded and XOR-swizzled by 16-byte
 // chunk so the MFMA operand reads are bank-conflict free; latent rows
-// (576 wide) are padded by two chunks instead: at 1184 bytes a row both the
-// key operand reads and the transposing value reads run at the full LDS rate
-// (256 bytes a clock; one chunk of padding, 1168 bytes, halves both).
+// (576 wide) have a stage layout and loader of their own, latent_tile.h.
 // ---------------------------------------------------------------------------
 enum RowMode { kPrefillGrouped = 0, kPrefillPerHead = 1, kDecodeLatent = 2, kPrefillFlat = 3 };
-
-typedef __attribute__((address_space(3))) uint8_t* lds_byte_ptr;
 
 // 16-byte global -> LDS copy per lane: lane i writes lds_wave_base + 16 i
 // (the LDS address goes in M0 and must be wave-uniform). Written as inline
@@ -582,7 +579,6 @@ __device__ __forceinline__ void dma16(const void* src, void* lds_wave_base) {
 // needs 5 wait states, and the compiler's hazard check does not look inside
 // inline assembly, so the block opens with them (s_nop 5: 6 wait states,
 // which also covers the M0 write before an LDS DMA).
-typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void dma16_buf(const i32x4& rsrc, uint32_t voffset, void* lds_wave_base) {
   const uint32_t m0 = uint32_t(reinterpret_cast<uintptr_t>((lds_byte_ptr)(lds_wave_base)));
   asm volatile("s_nop 5\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(voffset), "s"(rsrc),
@@ -601,34 +597,30 @@ __device__ __forceinline__ i32x4 uniform_rsrc(const void* base, uint32_t bytes) 
 template <int DQK, int DV, int NW, int RB, int BN, bool VALIAS, int NS>
 struct RowParCfg {
   static constexpr int DC = DQK / 32;
-  static constexpr int CPR = DQK / 8;                      // 16-byte chunks of a K row
-  static constexpr int CPRV = VALIAS ? 0 : DV / 8;         // of a separate V row
-  static constexpr int ROWB = VALIAS ? CPR + 2 : CPR;      // LDS K row stride, chunks
-  static constexpr int K_SLOTS = BN * ROWB;
+  static constexpr int CPR = DQK / 8;                      // 16-byte chunks of a K row, also in LDS
+  static constexpr int CPRV = DV / 8;                      // of a V row
+  static constexpr int K_SLOTS = BN * CPR;
   static constexpr int SLOTS = K_SLOTS + BN * CPRV;
   static constexpr int TI_RAW = (SLOTS + 63) / 64;         // 1 KB loads per tile
   static constexpr int TI = (TI_RAW + NW - 1) / NW * NW;
-  static constexpr int NI = TI / NW;                       // per wave per tile
-  // With two stages every tile wait drains all loads, so the loads past
-  // TI_RAW that only round TI up to the wave count are skipped and the stage
-  // holds TI_RAW KB (this is what lets two 4-wave latent work-groups share a
-  // CU's LDS). With more stages each wave counts NI loads per tile.
-  static constexpr int TI_USED = NS == 2 ? TI_RAW : TI;
-  static constexpr int STAGE = TI_USED * 1024;
+  // Per wave per tile; each wave counts NI loads per tile.
+  static constexpr int NI = VALIAS ? kLatentLoads : TI / NW;
+  // (Two latent stages are what lets two work-groups share a CU's LDS.)
+  static constexpr int STAGE = VALIAS ? kLatentStage : TI * 1024;
   static constexpr int V_OFF = K_SLOTS * 16;
   static constexpr int NT = NW * 64;
   static constexpr int NACC = DV / 16;
   static constexpr size_t LDS_BYTES = size_t(NS) * STAGE + kPageWin * 4;
   static_assert(BN % 32 == 0, "key tile is a multiple of 32");
   static_assert(VALIAS || K_SLOTS % 64 == 0, "separate K and V regions start on a load boundary");
+  static_assert(!VALIAS || (DQK == kLatentQK && DV == kLatentV && BN == kLatentBN && NW == 4), "latent tiles");
   static_assert((NS - 2) * NI < 64, "vmcnt range");
 };
 
 // Physical 16-byte chunk of logical chunk x in row r of an LDS tile.
-template <int DQK, bool VALIAS>
+template <int DQK>
 __device__ __forceinline__ int swz_k(int x, int r) {
-  if constexpr (VALIAS) return x;
-  else if constexpr (DQK == 128) return x ^ (r & 15);        // 256-byte rows
+  if constexpr (DQK == 128) return x ^ (r & 15);        // 256-byte rows
   else return x ^ ((r >> 1) & 7);   // 128-byte rows; 384-byte rows (odd rows start half a bank row on)
 }
 template <int DV>
@@ -657,26 +649,23 @@ __device__ __forceinline__ void wait_tiles(int ahead) {
   wait_vmem<0>();
 }
 
-// Tile loads of one work-group: BN keys of K rows (and of V rows unless V
-// aliases K) from the paged cache into one LDS stage, through 16-byte DMA
-// loads. Load instruction j of wave w fills 1 KB of a stage: lane slot
-// s = 64 * (w * NI + j) + lane is one 16-byte chunk of a K row
-// (s < K_SLOTS) or of a V row. Byte offsets split into a per-lane part fixed
-// for the whole launch and a per-tile part: a tile starts on a multiple of
-// BN keys, so in a tile that lies below key_end the slot of row r within its
-// page is r % P (pages of at most BN keys) or kb % P + r (larger pages).
-// s_pt holds the block-table entries of the current page window.
-template <int DQK, int DV, int NW, int BN, bool VALIAS, int NS, int P>
+// Tile loads of one work-group: BN keys of K rows and of V rows from the paged
+// cache into one LDS stage, through 16-byte DMA loads. Load instruction j of
+// wave w fills 1 KB of a stage: lane slot s = 64 * (w * NI + j) + lane is one
+// 16-byte chunk of a K row (s < K_SLOTS) or of a V row. Byte offsets split
+// into a per-lane part fixed for the whole launch and a per-tile part: a tile
+// starts on a multiple of BN keys, so in a tile that lies below key_end the
+// slot of row r within its page is r % P (pages of at most BN keys) or
+// kb % P + r (larger pages). s_pt holds the block-table entries of the current
+// page window.
+template <int DQK, int DV, int NW, int BN, int NS, int P>
 struct TileLoader {
-  using C = RowParCfg<DQK, DV, NW, 1, BN, VALIAS, NS>;
-  static_assert(VALIAS || P >= BN || (64 % C::CPR == 0 && P % (64 / C::CPR) == 0),
-                "a load instruction stays in one page");
-  // A whole tile whose load instructions each stay in one page (every row
-  // layout but the padded latent rows with pages of at most BN keys): the
-  // tile's pages are read once into scalar registers and every load goes
-  // through a buffer resource on its page, with the launch-fixed per-lane
-  // offsets; no per-tile vector address arithmetic.
-  static constexpr bool kUniformPage = !(VALIAS && P <= BN);
+  using C = RowParCfg<DQK, DV, NW, 1, BN, false, NS>;
+  static_assert(P >= BN || (64 % C::CPR == 0 && P % (64 / C::CPR) == 0), "a load instruction stays in one page");
+  // Every load instruction stays in one page: the pages of a whole tile are
+  // read once into scalar registers and every load goes through a buffer
+  // resource on its page, with the launch-fixed per-lane offsets; no per-tile
+  // vector address arithmetic.
   static constexpr int PPT = P <= BN ? BN / P : 1;   // pages per tile
 
   uint8_t* lds;
@@ -685,77 +674,51 @@ struct TileLoader {
   const uint8_t* kbase;
   const uint8_t* vbase;
   uint32_t ksp, kss, vsp, vss;
-  // Per-lane byte offsets of the loads, fixed for the launch. The two-stage
-  // latent form (four waves, ten loads each per tile, two work-groups per
-  // CU) forms them again at each tile instead of holding them: beside its
-  // accumulators and Q they would spill.
-  static constexpr bool kHoldOff = !(VALIAS && NS == 2);
-  uint32_t ld_lane_off[kHoldOff ? C::NI : 1];
+  uint32_t ld_lane_off[C::NI];   // per-lane byte offsets of the loads
 
   __device__ __forceinline__ TileLoader(const AttnParams& p, int head_kv, uint8_t* lds_, const int* s_pt_, int w_,
                                         int lane_, int key_end_)
       : lds(lds_), s_pt(s_pt_), w(w_), lane(lane_), key_end(key_end_) {
     kbase = reinterpret_cast<const uint8_t*>(p.kc.base + int64_t(head_kv) * p.kc.sh);
-    vbase = reinterpret_cast<const uint8_t*>((VALIAS ? p.kc.base : p.vc.base) +
-                                             int64_t(head_kv) * (VALIAS ? p.kc.sh : p.vc.sh));
+    vbase = reinterpret_cast<const uint8_t*>(p.vc.base + int64_t(head_kv) * p.vc.sh);
     ksp = uint32_t(p.kc.sp) * 2u;
     kss = uint32_t(p.kc.ss) * 2u;
-    vsp = uint32_t(VALIAS ? p.kc.sp : p.vc.sp) * 2u;
-    vss = uint32_t(VALIAS ? p.kc.ss : p.vc.ss) * 2u;
-    if constexpr (kHoldOff) {
+    vsp = uint32_t(p.vc.sp) * 2u;
+    vss = uint32_t(p.vc.ss) * 2u;
 #pragma unroll
-      for (int j = 0; j < C::NI; ++j) ld_lane_off[j] = form_lane_off(j, lane);
-    }
-  }
-  __device__ __forceinline__ uint32_t form_lane_off(int j, int ln) const {
-    int row;
-    uint32_t xoff;
-    slot_of(j, ln, row, xoff);
-    return (P <= BN ? uint32_t(row % P) : uint32_t(row)) * (is_v(j) ? vss : kss) + xoff;
-  }
-  __device__ __forceinline__ uint32_t lane_off(int j) const {
-    if constexpr (kHoldOff) {
-      return ld_lane_off[j];
-    } else {
-      int ln = lane;
-      asm volatile("" : "+v"(ln));   // keeps the arithmetic at the load, out of the loop
-      return form_lane_off(j, ln);
+    for (int j = 0; j < C::NI; ++j) {
+      int row;
+      uint32_t xoff;
+      slot_of(j, row, xoff);
+      ld_lane_off[j] = (P <= BN ? uint32_t(row % P) : uint32_t(row)) * (is_v(j) ? vss : kss) + xoff;
     }
   }
   // Whether load j of this wave fills V rows (wave-uniform).
-  __device__ __forceinline__ bool is_v(int j) const { return !VALIAS && (w * C::NI + j) * 64 >= C::K_SLOTS; }
-  // Row and byte offset within the row of the chunk lane slot s loads.
-  __device__ __forceinline__ void slot_of(int j, int ln, int& row, uint32_t& xoff) const {
+  __device__ __forceinline__ bool is_v(int j) const { return (w * C::NI + j) * 64 >= C::K_SLOTS; }
+  // Row and byte offset within the row of the chunk that the lane's slot of load j holds.
+  __device__ __forceinline__ void slot_of(int j, int& row, uint32_t& xoff) const {
     const int blk = w * C::NI + j;
-    const int s = blk * 64 + ln;
+    const int s = blk * 64 + lane;
     int x = 0;
     row = 0;
-    if constexpr (!kHoldOff) {   // branch-free: formed again at every tile
-      const int r = s / C::ROWB, pc = s - r * C::ROWB;
-      const bool in = s < C::K_SLOTS;
-      row = in ? r : 0;
-      x = in && pc < C::CPR ? pc : 0;
-    } else if (VALIAS || blk * 64 < C::K_SLOTS) {   // wave-uniform
+    if (blk * 64 < C::K_SLOTS) {   // wave-uniform
       if (s < C::K_SLOTS) {
-        row = s / C::ROWB;
-        const int pc = s % C::ROWB;
-        x = pc < C::CPR ? swz_k<DQK, VALIAS>(pc, row) : 0;
+        row = s / C::CPR;
+        x = swz_k<DQK>(s % C::CPR, row);
       }
     } else if (s < C::SLOTS) {
       const int s2 = s - C::K_SLOTS;
-      row = s2 / (C::CPRV > 0 ? C::CPRV : 1);
-      x = swz_v<DV>(s2 % (C::CPRV > 0 ? C::CPRV : 1), row);
+      row = s2 / C::CPRV;
+      x = swz_v<DV>(s2 % C::CPRV, row);
     }
     xoff = 16u * uint32_t(x);
   }
-  // Page of a slot within its tile (pages of at most BN keys): per lane for
-  // the padded latent rows; for unpadded rows one load instruction covers
-  // 64 / CPR whole rows of one page, so it is wave-uniform.
-  __device__ __forceinline__ int tile_page(int j, int row) const {
+  // Page of load j's rows within its tile (pages of at most BN keys): one load
+  // instruction covers 64 / CPR whole rows of one page, so it is wave-uniform.
+  __device__ __forceinline__ int tile_page(int j) const {
     if constexpr (P > BN) return 0;
-    if constexpr (VALIAS) return row / P;
     const int blk = w * C::NI + j;
-    const int row0 = blk * 64 < C::K_SLOTS ? blk * 64 / C::CPR : (blk * 64 - C::K_SLOTS) / (C::CPRV > 0 ? C::CPRV : 1);
+    const int row0 = blk * 64 < C::K_SLOTS ? blk * 64 / C::CPR : (blk * 64 - C::K_SLOTS) / C::CPRV;
     return __builtin_amdgcn_readfirstlane(row0 / P);
   }
   __device__ __forceinline__ void issue_whole(int kb, int st, int pt_base) const {
@@ -766,61 +729,63 @@ struct TileLoader {
     const uint32_t in_page = P > BN ? uint32_t(kb % P) : 0u;   // first slot of the tile in its page
 #pragma unroll
     for (int j = 0; j < C::NI; ++j) {
-      if constexpr (C::TI_USED < C::TI) {
-        if (w * C::NI + j >= C::TI_USED) break;   // wave-uniform
-      }
       const bool isv = is_v(j);
       const uint8_t* base = isv ? vbase : kbase;
       const uint32_t sp = isv ? vsp : ksp, ss = isv ? vss : kss;
-      const int tp = tile_page(j, 0);
+      const int tp = tile_page(j);
       int page = pg[0];
 #pragma unroll
       for (int t = 1; t < PPT; ++t) page = tp == t ? pg[t] : page;
       const i32x4 r = uniform_rsrc(base + (uint64_t(uint32_t(page)) * sp + in_page * ss), uint32_t(min(P, BN)) * ss);
-      dma16_buf(r, lane_off(j), sbase + (w * C::NI + j) * 1024);
+      dma16_buf(r, ld_lane_off[j], sbase + (w * C::NI + j) * 1024);
     }
   }
   // Issue this wave's loads of the key tile starting at kb into stage st.
   // Keys past key_end read the last key's row (masked later); padding slots
   // read a dummy row.
   __device__ __forceinline__ void issue(int kb, int st, int pt_base) const {
-    uint8_t* sbase = lds + st * C::STAGE;
-    const bool whole = kb + BN <= key_end;
-    if constexpr (kUniformPage) {
-      if (whole) {
-        issue_whole(kb, st, pt_base);
-        return;
-      }
+    if (kb + BN <= key_end) {
+      issue_whole(kb, st, pt_base);
+      return;
     }
+    uint8_t* sbase = lds + st * C::STAGE;
 #pragma unroll
     for (int j = 0; j < C::NI; ++j) {
-      if constexpr (C::TI_USED < C::TI) {
-        if (w * C::NI + j >= C::TI_USED) break;   // wave-uniform
-      }
       const bool isv = is_v(j);
       const uint8_t* base = isv ? vbase : kbase;
       const uint32_t sp = isv ? vsp : ksp, ss = isv ? vss : kss;
-      int pidx;
-      uint32_t off;
-      if (whole) {
-        int row = 0;
-        if constexpr (VALIAS && P <= BN) {
-          uint32_t xoff;
-          slot_of(j, lane, row, xoff);
-        }
-        pidx = kb / P - pt_base + tile_page(j, row);
-        off = P <= BN ? lane_off(j) : lane_off(j) + uint32_t(kb % P) * ss;
-      } else {
-        int row;
-        uint32_t xoff;
-        slot_of(j, lane, row, xoff);
-        const uint32_t key = uint32_t(min(kb + row, key_end - 1));
-        pidx = int(key / P) - pt_base;
-        off = (key % P) * ss + xoff;
-      }
-      const uint32_t page = uint32_t(s_pt[pidx]);
-      dma16(base + (uint64_t(page) * sp + off), sbase + (w * C::NI + j) * 1024);
+      int row;
+      uint32_t xoff;
+      slot_of(j, row, xoff);
+      const uint32_t key = uint32_t(min(kb + row, key_end - 1));
+      const uint32_t page = uint32_t(s_pt[int(key / P) - pt_base]);
+      dma16(base + (uint64_t(page) * sp + ((key % P) * ss + xoff)), sbase + (w * C::NI + j) * 1024);
     }
+  }
+};
+
+// The loader of a row layout. Latent tiles need no state per load: with a
+// padded row's chunks dealt out to the lanes, as above, ten per-lane offsets
+// (or, at page 16, addresses) a wave did not fit beside 128 accumulators and
+// Q, and each spilled register that is read back waits for every load in
+// flight. Two rows against 4000 keys on 64-row tiles: page 16 540 -> 137 us,
+// page 64 207 -> 139; 64-head decodes of 2000 keys 35 -> 21 and 26 -> 20.
+template <bool VALIAS, int DQK, int DV, int NW, int BN, int NS, int P>
+struct RowParLoader : TileLoader<DQK, DV, NW, BN, NS, P> {
+  using TileLoader<DQK, DV, NW, BN, NS, P>::TileLoader;
+};
+template <int DQK, int DV, int NW, int BN, int NS, int P>
+struct RowParLoader<true, DQK, DV, NW, BN, NS, P> : LatentLoader<P, false> {
+  const int* s_pt;
+  int key_end;
+  __device__ __forceinline__ RowParLoader(const AttnParams& p, int head_kv, uint8_t* lds, const int* s_pt_, int w,
+                                          int lane, int key_end_)
+      : LatentLoader<P, false>(p, head_kv, lds, w, lane), s_pt(s_pt_), key_end(key_end_) {}
+  __device__ __forceinline__ void issue(int kb, int st, int pt_base) const {
+    const int page = s_pt[min(kb + 8 * this->w, key_end - 1) / P - pt_base];
+    const i32x4 r = this->source(kb, key_end, __builtin_amdgcn_readfirstlane(page));
+#pragma unroll
+    for (int j = 0; j < kLatentLoads; ++j) this->load_one(r, st, j);
   }
 };
 
@@ -962,7 +927,7 @@ __device__ __forceinline__ void rowpar_body(const AttnParams& p, int item, int c
   }
   const u32x4 ones = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};   // bf16 1.0 x 8
 
-  const TileLoader<DQK, DV, NW, BN, VALIAS, NS, P> loader(p, head_kv, lds, s_pt, w, lane, key_end);
+  const RowParLoader<VALIAS, DQK, DV, NW, BN, NS, P> loader(p, head_kv, lds, s_pt, w, lane, key_end);
   auto issue = [&](int kb, int st, int pt_base) { loader.issue(kb, st, pt_base); };
 
   // Per-lane LDS byte offsets of the MFMA operand reads within a stage. The
@@ -970,18 +935,20 @@ __device__ __forceinline__ void rowpar_body(const AttnParams& p, int item, int c
   // the same for every 32-key chunk and 16-key block of a tile: chunk, block
   // and stage enter as immediate offsets.
   constexpr int CH = BN / 32;                      // 32-key chunks per tile
-  constexpr int KROW = C::ROWB * 16;               // LDS bytes per K row
-  constexpr int VROW = VALIAS ? KROW : C::CPRV * 16;
-  constexpr int NKO = VALIAS ? 1 : C::DC, NVO = VALIAS ? 1 : C::NACC;
+  constexpr int KROW = VALIAS ? kLatentRow : C::CPR * 16;   // LDS bytes from K row to K row
+  constexpr int VROW = VALIAS ? kLatentRow : C::CPRV * 16;
+  constexpr int NKO = VALIAS ? 3 : C::DC, NVO = VALIAS ? 1 : C::NACC;
   const int rowa0 = 4 * gq + (n >> 2);             // V row of the lane's first 4 keys
   const int cb = 8 * (n & 3);                      // byte offset of its 4 columns in a 32-byte block
   uint32_t k_off[NKO], v_off[NVO];
-  if constexpr (VALIAS) {
+  if constexpr (VALIAS) {   // the first 512 columns, and the two 64-byte parts of the last 64
     k_off[0] = uint32_t(n * KROW + 16 * gq);
+#pragma unroll
+    for (int c = 0; c < 2; ++c) k_off[1 + c] = uint32_t(kLatentTailOff + n * 128 + 16 * ((4 * c + gq) ^ ((n >> 1) & 7)));
     v_off[0] = uint32_t(rowa0 * VROW + cb);
   } else {
 #pragma unroll
-    for (int c = 0; c < C::DC; ++c) k_off[c] = uint32_t(n * KROW + 16 * swz_k<DQK, VALIAS>(4 * c + gq, n));
+    for (int c = 0; c < C::DC; ++c) k_off[c] = uint32_t(n * KROW + 16 * swz_k<DQK>(4 * c + gq, n));
 #pragma unroll
     for (int cv = 0; cv < C::NACC; ++cv) {
       const int x = 2 * cv + (cb >> 4);
@@ -991,8 +958,13 @@ __device__ __forceinline__ void rowpar_body(const AttnParams& p, int item, int c
   // Stage base (wave-uniform) + per-lane offset + an immediate; pointer
   // arithmetic so the constant part folds into the instruction's offset.
   auto kread = [&](const uint8_t* stage, int ch, int b, int c) {
-    const uint8_t* base = stage + (VALIAS ? k_off[0] : k_off[c]);
-    return *reinterpret_cast<const u32x4*>(base + ((32 * ch + 16 * b) * KROW + (VALIAS ? 64 * c : 0)));
+    if constexpr (VALIAS) {
+      if (c >= kLatentV / 32)
+        return *reinterpret_cast<const u32x4*>(stage + k_off[1 + c - kLatentV / 32] + (32 * ch + 16 * b) * 128);
+      return *reinterpret_cast<const u32x4*>(stage + k_off[0] + ((32 * ch + 16 * b) * KROW + 64 * c));
+    } else {
+      return *reinterpret_cast<const u32x4*>(stage + k_off[c] + (32 * ch + 16 * b) * KROW);
+    }
   };
   auto vread = [&](const uint8_t* stage, int ch, int half, int cv) {
     const uint8_t* base = stage + (VALIAS ? v_off[0] : v_off[cv]);
@@ -1030,8 +1002,8 @@ __device__ __forceinline__ void rowpar_body(const AttnParams& p, int item, int c
         // The compiler places each operand read right before its product
         // and waits for it there, a full LDS latency per product: reads run
         // KD products ahead instead, held in place by the scheduling
-        // barriers (64-head mixed latent step, with the row padding above:
-        // 267 -> 215 us, its decodes now 44 us).
+        // barriers (with rows free of bank conflicts, 64-head mixed latent
+        // step: 267 -> 215 us).
         constexpr int KD = 4, NK = 2 * C::DC;
         u32x4 kb[KD];
 #pragma unroll
@@ -1270,7 +1242,7 @@ __device__ __forceinline__ void rowpar_body(const AttnParams& p, int item, int c
 }
 
 template <int DQK, int DV, int NW, int RB, int BN, bool VALIAS, int MODE, int P, int NS, int TB>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(VALIAS && NS == 2 ? 2 : NW / 4)))
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(VALIAS ? 2 : NW / 4)))
 void rowpar_kernel(AttnParams p) {
   // Work-group -> (item, column). Decode pieces launch longest first; prefill
   // tiles are listed that way. Grouped-query prefill with a column count

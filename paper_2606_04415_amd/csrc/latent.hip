@@ -22,32 +22,24 @@
 
 #include "device_common.h"
 #include "kernels.h"
+#include "latent_tile.h"
 
 namespace flexattn {
 
 namespace {
 
 typedef __bf16 short2v __attribute__((ext_vector_type(2)));
-typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) uint8_t* lds_byte_ptr;
 
-constexpr int kQK = 576, kV = 512;
-constexpr int kBN = 32;                  // keys of a tile
+constexpr int kQK = kLatentQK, kV = kLatentV;
+constexpr int kBN = kLatentBN;
 constexpr int kNW = 4;                   // waves, 32 query rows each
 constexpr int kDC = kQK / 16;            // 16-dim chunks of the score products
 constexpr int kACC = kV / 32;            // 32-column blocks of the values
 constexpr int kStages = 4;
-// A stage holds the first 512 columns of its keys, one row per 1 KB load, and
-// after them the last 64 columns, eight rows per load (36 loads a tile, none
-// for padding). At a row stride of 1056 bytes, with neighbouring 16-byte
-// chunks swapped in rows 16 to 31, both products' operand reads are free of
-// bank conflicts (233 / 200 bytes a clock for key / transposing value reads;
-// without the swap 123 for the keys). The 128-byte rows of the
-// last columns are XOR-swizzled by 16-byte chunk.
-constexpr int kRow = 1056;
-constexpr int kTailOff = kBN * kRow;
-constexpr int kStage = kTailOff + kBN * 128;
-constexpr int kLoads = 9;                // loads of a wave per tile
+// Neighbouring 16-byte chunks are swapped in rows 16 to 31, without which the
+// 32 rows of a key operand read conflict (key / transposing value reads 233 /
+// 200 bytes a clock; without the swap 123 for the keys).
+constexpr int kRow = kLatentRow, kTailOff = kLatentTailOff, kStage = kLatentStage, kLoads = kLatentLoads;
 // A row's maximum moves only when a tile raises it by more than this many
 // log2 units, as in the other row-parallel kernels. A fresher maximum is not
 // only a matter of range: a row's largest probability is exactly 1 while it
@@ -233,41 +225,9 @@ void latent_kernel(AttnParams p) {
       o[a][r] = z;
     }
 
-  const uint8_t* kbase = reinterpret_cast<const uint8_t*>(p.kc.base + int64_t(head_kv) * p.kc.sh);
-  const uint32_t ksp = uint32_t(p.kc.sp) * 2u, kss = uint32_t(p.kc.ss) * 2u;
-
-  // Loads of a tile: the wave's 8 rows lie in one page, so one resource on
-  // the page serves all nine. Lane i of a row load takes 16-byte chunk i of
-  // the row (i ^ 1 in rows 16 to 31); of the tail load, chunk
-  // 64 + ((i & 7) ^ swizzle) of row i >> 3. The record count ends with the
-  // row of the tile's last key (a whole row past its start: the slot stride
-  // may be less than a row), so what is read past it reads as zeros and
-  // touches no memory. Tiles past the window get empty resources: their loads
-  // are issued all the same between the score products, where a branch per
-  // load would cost more.
-  const uint32_t ld_row = 16u * uint32_t(lane ^ (w >> 1));
-  const uint32_t ld_tail =
-      uint32_t(lane >> 3) * kss + 1024u + 16u * uint32_t((lane & 7) ^ (((8 * w + (lane >> 3)) >> 1) & 7));
-  const uint32_t lds0 = uint32_t(reinterpret_cast<uintptr_t>((lds_byte_ptr)lds)) + uint32_t(8 * w) * kRow;
-  auto source = [&](int kb, int end, int page) {
-    const int g0 = kb + 8 * w;
-    const uint64_t a = reinterpret_cast<uint64_t>(kbase + (uint64_t(uint32_t(page)) * ksp + uint32_t(g0 % P) * kss));
-    const int rows = min(8, end - g0);
-    i32x4 r = {__builtin_amdgcn_readfirstlane(int32_t(uint32_t(a))),
-               __builtin_amdgcn_readfirstlane(int32_t(uint32_t(a >> 32) & 0xFFFFu)),
-               __builtin_amdgcn_readfirstlane(rows > 0 ? int32_t(uint32_t(rows - 1) * kss + 2 * kQK) : 0), kBufferFlags};
-    // A vector instruction's scalar result needs 5 wait states before a
-    // memory instruction reads it; the loads below are opaque to the compiler.
-    asm volatile("s_nop 4" : "+s"(r));
-    return r;
-  };
-  auto load_one = [&](const i32x4& rsrc, int st, int j) {
-    const uint32_t dst = lds0 + uint32_t(st) * kStage + (j < 8 ? uint32_t(j) * kRow : uint32_t(kTailOff + w * 1024 - 8 * w * kRow));
-    const uint32_t off = j < 8 ? ld_row + uint32_t(j) * kss : ld_tail;
-    asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(off), "s"(rsrc),
-                 "{m0}"(__builtin_amdgcn_readfirstlane(dst))
-                 : "memory");
-  };
+  // Tiles past the window get empty resources: their loads are issued all the
+  // same between the score products, where a branch per load would cost more.
+  const LatentLoader<P, true> loader(p, head_kv, lds, w, lane);
 
   // Operand reads: stage base + per-lane offset + immediate. Value block cv
   // covers 32 columns, vcol(cv) + 0..15 in lanes n < 16 and + 64..79 in the
@@ -395,9 +355,9 @@ void latent_kernel(AttnParams p) {
     // Page of the wave's rows of tile t (rows past the window: its last page).
     auto page_at = [&](int t) { return s_pt[min(wk0 + t * kBN + 8 * w, wk1 - 1) / P - pt_base]; };
     auto load_tile = [&](int t) {
-      const i32x4 s = source(wk0 + t * kBN, wk1, __builtin_amdgcn_readfirstlane(page_at(t)));
+      const i32x4 s = loader.source(wk0 + t * kBN, wk1, __builtin_amdgcn_readfirstlane(page_at(t)));
 #pragma unroll
-      for (int j = 0; j < kLoads; ++j) load_one(s, t & (kStages - 1), j);
+      for (int j = 0; j < kLoads; ++j) loader.load_one(s, t & (kStages - 1), j);
     };
     // Tile t + 1 of iteration t (or tile 0 here) has landed once at most the
     // loads of the tiles after it are outstanding. Close to the end those may
@@ -433,8 +393,8 @@ void latent_kernel(AttnParams p) {
         i32x4 src;
         scores(stage_of(t + 1), s, [&](auto ic) {
           constexpr int i = ic;
-          if constexpr (i == 1) src = source(wk0 + (t + 3) * kBN, wk1, __builtin_amdgcn_readfirstlane(pgv));
-          if constexpr (i % 4 == 2) load_one(src, (t + 3) & (kStages - 1), i / 4);
+          if constexpr (i == 1) src = loader.source(wk0 + (t + 3) * kBN, wk1, __builtin_amdgcn_readfirstlane(pgv));
+          if constexpr (i % 4 == 2) loader.load_one(src, (t + 3) & (kStages - 1), i / 4);
           if constexpr (i % 4 == 1 && i < 32) prob_lo(i / 4);
           if constexpr (i % 4 == 3 && i < 32) prob_hi(i / 4);
         });

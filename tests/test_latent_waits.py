@@ -77,3 +77,18 @@ def test_a_read_ahead_of_the_wait_is_found(kernels):
     lines = list(next(iter(kernels.values())))
     last = max(i for i, l in enumerate(lines) if l == "s_nop 15" and lines[i - 1] == "s_nop 15")
     assert early_reads(lines[:last - 1] + lines[last + 1:])
+
+
+def test_latent_kernels_hold_everything_in_registers(tmp_path):
+    """A spilled register that is read back inside the tile loop waits for every
+    load in flight, which undoes the loads ahead."""
+    spills = {}
+    for src in ("attention.hip", "latent.hip"):
+        out = tmp_path / "k.s"
+        subprocess.run([B.hipcc()] + B.common_flags() + ["--cuda-device-only", "-S", f"{B.CSRC}/{src}", "-o", str(out)],
+                       check=True, capture_output=True, timeout=300)
+        for m in re.finditer(r"^(_ZN\S*(?:rowpar_kernelILi576|latent_kernel)\S*):.*?; ScratchSize: (\d+)", out.read_text(),
+                             re.S | re.M):
+            spills[m[1]] = int(m[2])
+    assert len(spills) == 8   # 64 and 128 rows, decode and prefill, pages of 16 and 64
+    assert not any(spills.values()), spills
