@@ -148,15 +148,13 @@ def cpu_baseline(b, seconds_target=15.0):
 
 
 TRAFFIC_FILE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "profiles", "traffic.json")
-KERNEL_SOURCE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_2606_04415_amd", "csrc",
-                             "attention.hip")
 
 
 def kernel_source_hash():
-    """Hash of the kernel source's code (comments and whitespace removed),
+    """Hash of the kernel sources' code (comments and whitespace removed),
     the key of the committed counter summary."""
     from paper_2606_04415_amd.profsum import source_hash
-    return source_hash(KERNEL_SOURCE)
+    return source_hash()
 
 
 def measured_traffic(workload, kernel):
@@ -253,9 +251,18 @@ def timed_dist(mean, per):
 
 def prefill_kernel_name(bm, head_dim_qk):
     """The kernel a plan's prefill tiles run on."""
-    if head_dim_qk in (64, 128) and bm == 128:
-        return "flat_prefill_kernel"
+    if head_dim_qk == 192:
+        return "perhead_prefill_kernel"
+    if bm == 128:
+        return "latent_kernel (prefill)" if head_dim_qk == 576 else "flat_prefill_kernel"
     return "rowpar_kernel (prefill)"
+
+
+def decode_kernel_name(num_q_heads, head_dim_qk):
+    """The kernel a plan's decode pieces run on: latent heads in groups of 128, or of 64 where 128 does not divide them."""
+    if head_dim_qk != 576:
+        return "decode_gqa_kernel"
+    return "latent_kernel (decode)" if num_q_heads % 128 == 0 else "rowpar_kernel (latent decode)"
 
 
 def roof(bound, achieved, unit):
@@ -302,8 +309,7 @@ def bench_config(name, steps, warmup, settle_ms, pools):
             r["GBps"] = round(dec_b / (d["mean"] * 1e-6) / 1e9, 1)
             r["roofline"] = roof("hbm", r["GBps"], "GB/s")
             r["roofline"]["traffic"] = measured_traffic(name, "decode")
-            r["kernel"] = "decode_gqa_kernel + merge_kernel" if w.head_dim_qk != 576 else \
-                "rowpar_kernel (latent decode) + merge_kernel"
+            r["kernel"] = decode_kernel_name(w.num_q_heads, w.head_dim_qk) + " + merge_kernel"
             r["algorithmic_bytes"] = dec_b
             if w.head_dim_qk == 576:   # latent decode sits near the ridge: its MFMA side too
                 fl = work["decode"]["flops"]
@@ -554,7 +560,7 @@ def main():
         achieved = dec_share_bytes / (c_dec * 1e-3) / 1e9
         roof_ = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                  "frac": round(achieved / HBM_PEAK_GBPS, 4), "traffic": share_traffic,
-                 "kernel": "decode_gqa_kernel" if w.head_dim_qk != 576 else "rowpar_kernel (latent decode)",
+                 "kernel": decode_kernel_name(w.num_q_heads, w.head_dim_qk),
                  "algorithmic_bytes_per_launch": round(dec_share_bytes), "avg_launch_us": round(c_dec * 1e3, 2),
                  "cus": cd}
         if tail_frac and share_traffic is not None:

@@ -4,7 +4,7 @@ Kernel statistics (``--kernel-trace --stats``) become a markdown table;
 per-dispatch FETCH_SIZE / WRITE_SIZE counters (``--pmc``), scaled by what the
 same counters read for a device copy of known size (``bench.py
 --copy-calibration``), become HBM bytes per launch in ``traffic.json``, keyed
-to the kernel source they were measured on (bench.py drops them once the
+to the kernel sources they were measured on (bench.py drops them once the
 kernels change).
 
     python -m paper_2606_04415_amd.profsum stats <kernel_stats.csv> <title> <command> > profiles/x.md
@@ -22,7 +22,8 @@ import re
 import sys
 from collections import defaultdict
 
-KERNEL_SOURCE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc", "attention.hip")
+KERNEL_SOURCES = tuple(os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc", f)
+                       for f in ("attention.hip", "latent.hip", "latent_tile.h", "device_common.h"))
 COPY_BYTES = 1 << 30
 
 
@@ -34,9 +35,13 @@ def code_text(src: str) -> str:
     return " ".join(src.split())
 
 
-def source_hash(path: str = KERNEL_SOURCE) -> str:
-    with open(path, encoding="utf-8") as f:
-        return hashlib.sha256(code_text(f.read()).encode()).hexdigest()[:16]
+def source_hash(*paths: str) -> str:
+    """Of the code of the given files, or of all sources of the attention kernels."""
+    h = hashlib.sha256()
+    for path in paths or KERNEL_SOURCES:
+        with open(path, encoding="utf-8") as f:
+            h.update(code_text(f.read()).encode() + b"\0")
+    return h.hexdigest()[:16]
 
 
 def stats_table(path, title, command):
@@ -53,14 +58,17 @@ def stats_table(path, title, command):
 
 def kernel_role(name):
     """decode / prefill / merge for the library's kernels, None for others.
-    rowpar_kernel's seventh template argument is its row layout (2: latent
-    decode rows, else prefill tiles)."""
+    latent_kernel's first template argument is whether it decodes;
+    rowpar_kernel's seventh is its row layout (2: latent decode rows, else
+    prefill tiles)."""
     if "merge_kernel" in name:
         return "merge"
     if "decode_gqa_kernel" in name:
         return "decode"
-    if "flat_prefill_kernel" in name:
+    if "flat_prefill_kernel" in name or "perhead_prefill_kernel" in name:
         return "prefill"
+    if "latent_kernel<" in name:
+        return "decode" if "latent_kernel<true" in name else "prefill"
     if "rowpar_kernel<" in name:
         targs = name.split("rowpar_kernel<", 1)[1].split(">", 1)[0].split(",")
         return "decode" if len(targs) > 6 and targs[6].strip() == "2" else "prefill"

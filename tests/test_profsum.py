@@ -2,6 +2,8 @@
 per-workload HBM-traffic file (counter CSVs written here, no GPU)."""
 import csv
 import json
+import pathlib
+import re
 import types
 
 from paper_2606_04415_amd import profsum
@@ -13,8 +15,12 @@ def test_kernel_roles():
     assert r("void flexattn::merge_kernel<512>(flexattn::AttnParams)") == "merge"
     assert r("void flexattn::flat_prefill_kernel<128, 4, 2, 32, 16, 3, 3>(flexattn::AttnParams)") == "prefill"
     # rowpar_kernel's seventh template argument is the row layout: 2 = latent decode rows
-    assert r("void flexattn::rowpar_kernel<576, 512, 8, 1, 32, true, 2, 64, 3, 1>(flexattn::AttnParams)") == "decode"
-    assert r("void flexattn::rowpar_kernel<576, 512, 8, 1, 32, true, 1, 64, 3, 1>(flexattn::AttnParams)") == "prefill"
+    assert r("void flexattn::rowpar_kernel<576, 512, 4, 1, 32, true, 2, 64, 2, 1>(flexattn::AttnParams)") == "decode"
+    assert r("void flexattn::rowpar_kernel<576, 512, 4, 1, 32, true, 1, 64, 2, 1>(flexattn::AttnParams)") == "prefill"
+    # latent_kernel's first is whether it decodes
+    assert r("void flexattn::latent_kernel<true, 64>(flexattn::AttnParams)") == "decode"
+    assert r("void flexattn::latent_kernel<false, 16>(flexattn::AttnParams)") == "prefill"
+    assert r("void flexattn::perhead_prefill_kernel<192, 128, 4, 2, 32, 64, 3, 2>(flexattn::AttnParams)") == "prefill"
     assert r("void flexattn::rowpar_kernel<128, 128, 16, 1, 64, false, 0, 16, 3, 2>(flexattn::AttnParams)") == "prefill"
     assert r("__amd_rocclr_copyBuffer") is None
 
@@ -75,3 +81,31 @@ def test_source_hash_ignores_comments_only(tmp_path):
     c.write_text("__global__ void k(int* p) { p[0] = 2; }\n")
     assert profsum.source_hash(str(a)) == profsum.source_hash(str(b))
     assert profsum.source_hash(str(a)) != profsum.source_hash(str(c))
+
+
+def test_source_hash_covers_every_kernel_source(tmp_path):
+    """Every file that holds device code of the attention kernels is part of
+    the key: the counters of latent_kernel go stale with latent.hip."""
+    from paper_2606_04415_amd.build import CSRC
+    names = {p.rsplit("/", 1)[1] for p in profsum.KERNEL_SOURCES}
+    device = {f.name for f in pathlib.Path(CSRC).iterdir()
+              if re.search(r"__global__|__device__ __forceinline__", f.read_text())}
+    assert device - names == {"kv_append.hip"}   # no attention kernel there
+    a, b = tmp_path / "a.hip", tmp_path / "b.hip"
+    a.write_text("int a;")
+    b.write_text("int b;")
+    both = profsum.source_hash(str(a), str(b))
+    b.write_text("int c;")
+    assert profsum.source_hash(str(a), str(b)) != both
+
+
+def test_bench_names_the_kernels_that_run():
+    import bench
+    assert bench.decode_kernel_name(128, 576) == "latent_kernel (decode)"
+    assert bench.decode_kernel_name(64, 576) == "rowpar_kernel (latent decode)"
+    assert bench.decode_kernel_name(28, 128) == "decode_gqa_kernel"
+    assert bench.prefill_kernel_name(128, 576) == "latent_kernel (prefill)"
+    assert bench.prefill_kernel_name(64, 576) == "rowpar_kernel (prefill)"
+    assert bench.prefill_kernel_name(128, 192) == "perhead_prefill_kernel"
+    assert bench.prefill_kernel_name(128, 64) == "flat_prefill_kernel"
+    assert bench.prefill_kernel_name(32, 128) == "rowpar_kernel (prefill)"
