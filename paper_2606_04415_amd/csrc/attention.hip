@@ -113,8 +113,6 @@ constexpr int kPageWin = 512;
 // stale max (so they stay below 2^8) and the accumulators are left alone.
 constexpr float kRescaleThreshold = 8.0f;
 
-__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
-
 __device__ __forceinline__ bool wave_any(bool pred) { return __builtin_amdgcn_ballot_w64(pred) != 0; }
 
 // Online-softmax step of one 16-row block over one 32-key chunk.
@@ -1341,8 +1339,7 @@ static hipError_t launch_fused_t(const AttnParams& pp, const AttnParams& pd, con
   const size_t dec_lds = 8 * size_t(decode_kstage_bytes<D>()) + size_t(RPW) * size_t(std::max(pd.range_pages, 1)) * 4;
   const size_t lds = C::LDS_BYTES > dec_lds ? C::LDS_BYTES : dec_lds;
   auto kern = fused_kernel<D, P, RPW>;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+  const hipError_t e = set_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(n_order), dim3(512), lds, stream, pp, pd, order);
   return hipGetLastError();
@@ -1459,13 +1456,6 @@ __global__ void fill_zero_kernel(uint32_t* p, size_t words) {
 // ---------------------------------------------------------------------------
 // Launchers.
 // ---------------------------------------------------------------------------
-// Allow a kernel the dynamic LDS it launches with. The attribute is set on
-// every launch (it is a cheap host-side call), so it holds on whichever device
-// is current and a transient failure is not remembered.
-static hipError_t set_dynamic_lds(const void* kern, size_t bytes) {
-  return hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));
-}
-
 template <int DQK, int DV, int NW, int RB, int BN, bool VALIAS, int MODE, int P, int NS, int TB = 1>
 static hipError_t launch_rowpar(const AttnParams& p, dim3 grid, hipStream_t stream) {
   using C = RowParCfg<DQK, DV, NW, RB, BN, VALIAS, NS>;
@@ -1611,10 +1601,10 @@ static hipError_t launch_prefill_p(const AttnParams& p, int dqk, int bm, dim3 gr
     return dqk == 128 ? launch_prefill_grouped<128, P>(q, bm, grid, stream)
                       : launch_prefill_grouped<64, P>(q, bm, grid, stream);
   }
-  // One work-group per (tile, query head), a wave per 16 rows (32 with the
-  // heads split out); XCD-aware 1-D grid when the head count is a multiple
-  // of 8. Latent 64-row tiles run
-  // four waves over two LDS stages, so that two work-groups share a CU
+  // One work-group per (tile, query head); XCD-aware 1-D grid when the head
+  // count is a multiple of 8, as it always is for latent rows. Latent 128-row
+  // tiles and split-out heads take 32 rows a wave; latent 64-row tiles take
+  // 16, four waves over two LDS stages, so that two work-groups share a CU
   // (with three stages one work-group of four waves held the CU alone: 1.8x
   // slower).
   if (p.grid_y % 8 == 0) {
@@ -1628,8 +1618,6 @@ static hipError_t launch_prefill_p(const AttnParams& p, int dqk, int bm, dim3 gr
     }
     return hipErrorInvalidValue;
   }
-  if (dqk == 576 && bm == 128) return launch_latent128(p, false, grid, stream);
-  if (dqk == 576 && bm == 64) return launch_rowpar<576, 512, 4, 1, 32, true, kPrefillPerHead, P, 2>(p, grid, stream);
   // Heads split out (keys 192, values 128): one work-group per (128-token
   // tile, query head), four waves of 32 rows (two 16-row blocks each, so
   // every K/V operand read from LDS feeds two products); 32-key tiles in

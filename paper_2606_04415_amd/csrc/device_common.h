@@ -71,6 +71,8 @@ __device__ __forceinline__ int32_t scalar_word(const int32_t* base, int idx) {
 // before a pipelined loop, so loop-carried wait tracking starts clean).
 __device__ __forceinline__ void wait_vmem_all() { wait_vmem<0>(); }
 
+__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+
 // Pack two floats into two bf16 (round to nearest even) in one dword, lo first.
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));

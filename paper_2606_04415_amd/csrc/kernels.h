@@ -1,5 +1,5 @@
-// Kernel parameter blocks and launchers (host-callable, defined in attention.hip
-// and kv_append.hip).
+// Kernel parameter blocks and launchers (host-callable, defined in attention.hip,
+// latent.hip and kv_append.hip).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -38,6 +38,13 @@ struct AttnParams {
   int32_t xcd_remap;      // prefill: 1-D grid mapped so each XCD serves one column
   float scale_log2;       // sm_scale * log2(e)
 };
+
+// Allow a kernel the dynamic LDS it launches with. The attribute is set on
+// every launch (it is a cheap host-side call), so it holds on whichever device
+// is current and a transient failure is not remembered.
+inline hipError_t set_dynamic_lds(const void* kern, size_t bytes) {
+  return hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));
+}
 
 hipError_t launch_decode(const AttnParams& p, int head_dim_qk, bool has_splits, hipStream_t stream);
 // The split-K merge alone (after decode launches that skipped it).

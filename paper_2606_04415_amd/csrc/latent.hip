@@ -94,8 +94,6 @@ __device__ __forceinline__ void accumulators_ready(f32x16 (&o)[N]) {
   for (int a = 0; a < N; ++a) asm volatile("" : "+a"(o[a]));
 }
 
-__device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
-
 // One element of an accumulator (read this way because the compiler moves whole
 // accumulators to vector registers for plain reads of their elements).
 __device__ __forceinline__ float acc_read(float a) {
@@ -292,7 +290,7 @@ void latent_kernel(AttnParams p) {
     const bool need = cmax > m + kRescale;
     const bool moved = need && m != -FLT_MAX;   // before its first visible key a row's accumulators are zero
     const float m_new = need ? cmax : m;
-    alpha = exp2_fast(m - m_new);   // 1 if unchanged
+    alpha = fast_exp2(m - m_new);   // 1 if unchanged
     m = m_new;
     l *= alpha;   // the sums of the tiles before; the accumulators follow in do_rescale
     moved_rows = uint32_t(__builtin_amdgcn_ballot_w64(moved));   // (both halves hold the same rows)
@@ -302,9 +300,9 @@ void latent_kernel(AttnParams p) {
   // Probabilities 2^x as the bf16 A operand of P V, and their row sums.
   u32x4 pop[2];
   float pe;
-  auto prob_lo = [&](int j) { pe = exp2_fast(x[2 * j]); };
+  auto prob_lo = [&](int j) { pe = fast_exp2(x[2 * j]); };
   auto prob_hi = [&](int j) {   // j = 0..7: keys of registers 2j, 2j + 1
-    const uint32_t pk = pack_bf16x2(pe, exp2_fast(x[2 * j + 1]));
+    const uint32_t pk = pack_bf16x2(pe, fast_exp2(x[2 * j + 1]));
     pop[j >> 2][j & 3] = pk;
     l = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(short2v, pk), __builtin_bit_cast(short2v, 0x3F803F80u), l, false);
   };
@@ -513,8 +511,7 @@ void latent_kernel(AttnParams p) {
 template <bool DECODE, int P>
 static hipError_t launch_latent_t(const AttnParams& p, dim3 grid, hipStream_t stream) {
   auto kern = latent_kernel<DECODE, P>;
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+  const hipError_t e = set_dynamic_lds(reinterpret_cast<const void*>(kern), kLds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, grid, dim3(kNW * 64), kLds, stream, p);
   return hipGetLastError();

@@ -168,8 +168,8 @@ extern "C" int flex_attn_plan(const flex_attn_shape* shape, const flex_attn_plan
   // Decode work-groups per key range: one per group of up to 8 KV heads for
   // grouped-query attention (a work-group then reads whole slot rows, which
   // spreads its stream over every memory channel); for the latent layout one
-  // per 128 query heads (eight waves of 16 heads share each key tile), or per
-  // 64 when 128 does not divide Hq.
+  // per 128 query heads (four waves of 32 heads share each key tile), or per
+  // 64 (four of 16) when 128 does not divide Hq.
   const int32_t heads_per_wg = std::min(sh.num_kv_heads, kDecodeHeadsPerWG);
   const int32_t latent_rows = sh.num_q_heads % kLatentRowsPerWGWide == 0 ? kLatentRowsPerWGWide : kLatentRowsPerWG;
   const int32_t W = latent ? sh.num_q_heads / latent_rows : int32_t(cdiv(sh.num_kv_heads, heads_per_wg));
