@@ -12,8 +12,8 @@
 // ahead, the exponentials of a tile are issued between the score products of
 // the next one, and the row maxima of the next tile between the value
 // products of this one. Against eight waves of 16 rows: 4096-token prompt of
-// 128 heads 2402 -> 2005 us (1.17 PFLOP/s; a loop of nothing but these
-// products reaches 1.84), 256 decodes over 1024 to 16384 keys 759 -> 718 us.
+// 128 heads 2402 -> 2070 us (1.13 PFLOP/s; a loop of nothing but these
+// products reaches 1.84), 256 decodes over 1024 to 16384 keys 759 -> 730 us.
 #include <float.h>
 #include <math.h>
 
